@@ -423,6 +423,16 @@ __global__ __launch_bounds__(256) void block_reduce_kernel(double* part, i64 p_b
 // A_ij -= L_ik L_jk^T and X_ij -= L_ik X_kj, X = L^{-1} being built beside L.  The update of the next
 // diagonal tile and its factorisation run on wave 0 under the other waves' updates.
 // b = 28, 64, 96: 9, 17, 31 us a call, launch included (12, 28, 51 with two columns eliminated per barrier).
+//
+// A Gram of numerically low rank (the Ising model deep in a phase) gives blocks of fewer directions than columns.
+// The shift carries the first pass over that; in the plain passes after it a column that depends on the ones
+// before it has a pivot that is rounding only, of either sign, and its reciprocal root would fill the tiles
+// after it with infinities.  Where the caller can replace columns (tiny), such a column is dropped instead: its row
+// of L^{-1} and its column of L are zero, and the block gets hash noise in its place, which the next pass
+// orthonormalises.  kDependent: that far below the column's squared norm the pivot is rounding (96 columns:
+// 2^-53 x 96 = 2^-46.4, and the explicit inverses of the tiles add to it).
+constexpr double kDependent = 0x1p-42;
+
 __device__ inline double rsqrt64(double d) {
     double r = __builtin_amdgcn_rsq(d);
     r *= 1.5 - 0.5 * d * r * r;
@@ -438,12 +448,15 @@ __device__ inline double row_bcast(double v) {   // the value of lane J of this 
     return __longlong_as_double(((long long)hi << 32) | (unsigned)lo);
 }
 
-// column K of a 16 x 16 tile: row i = lane mod 16 in a, columns 4 (lane / 16) + m of the inverse in x
+// column K of a 16 x 16 tile: row i = lane mod 16 in a, columns 4 (lane / 16) + m of the inverse in x.  Bit K of bad:
+// its pivot is not above `least` (of row i, 0 unless columns are dropped) or not finite.
 template <int K, int... J>
-__device__ inline void diag_column(double (&a)[16], double (&x)[4], int i, bool& bad, std::integer_sequence<int, J...>) {
+__device__ inline void diag_column(double (&a)[16], double (&x)[4], int i, double least, bool drop, unsigned& bad,
+                                   std::integer_sequence<int, J...>) {
     double d = row_bcast<K>(a[K]);
-    if (!(d > 0.0) || !isfinite(d)) { bad = true; d = 1e-300; }
-    const double r = rsqrt64(d);
+    const bool no = !(d > row_bcast<K>(least)) || !isfinite(d);
+    if (no) { bad |= 1u << K; d = 1e-300; }
+    const double r = no && drop ? 0.0 : rsqrt64(d);
     const double l = i > K ? a[K] * r : 0.0;
     ((a[K + 1 + J] -= l * row_bcast<K + 1 + J>(l)), ...);
 #pragma unroll
@@ -453,8 +466,9 @@ __device__ inline void diag_column(double (&a)[16], double (&x)[4], int i, bool&
     }
 }
 template <int... K>
-__device__ inline void diag_columns(double (&a)[16], double (&x)[4], int i, bool& bad, std::integer_sequence<int, K...>) {
-    (diag_column<K>(a, x, i, bad, std::make_integer_sequence<int, 15 - K>()), ...);
+__device__ inline void diag_columns(double (&a)[16], double (&x)[4], int i, double least, bool drop, unsigned& bad,
+                                    std::integer_sequence<int, K...>) {
+    (diag_column<K>(a, x, i, least, drop, bad, std::make_integer_sequence<int, 15 - K>()), ...);
 }
 
 template <int T>
@@ -465,7 +479,8 @@ __global__ __launch_bounds__(256) void block_chol_kernel(const double* __restric
     // rows 4 modulo 32 doubles apart: the 16 rows x 4 columns of an operand read fall on different banks
     constexpr int N = 16 * T, LD = N <= 36 ? 36 : (N <= 68 ? 68 : 100);
     __shared__ double A[N * LD], X[N * LD];
-    __shared__ double inv[N], dist[4];
+    __shared__ double inv[N], dist[4];   // inv, not scaled: the least pivots
+    __shared__ unsigned gone_of[T];      // columns of a diagonal tile that were dropped
     const int tid = threadIdx.x, z = blockIdx.x, lane = tid & 63, w = tid >> 6, lr = lane >> 4, lc = lane & 15;
     const int ty = tid >> 4, tx = tid & 15;
     if (skip && skip[z]) {
@@ -475,6 +490,7 @@ __global__ __launch_bounds__(256) void block_chol_kernel(const double* __restric
     part += z * p_bs;
     Rinv += z * r_bs;
     if (tiny) tiny += z * t_bs;
+    const bool drop = tiny && !scaled;
     const int bb = b * b;
     auto sum = [&](int i) {
         double v[kConsumerParts], s = 0.0;
@@ -517,6 +533,7 @@ __global__ __launch_bounds__(256) void block_chol_kernel(const double* __restric
             }
             const double e = v - (r == c ? 1.0 : 0.0);
             far += e * e;
+            if (r == c && !scaled) inv[r] = drop ? kDependent * v : 0.0;
             A[r * LD + c] = v;
             X[r * LD + c] = 0.0;
         }
@@ -530,11 +547,15 @@ __global__ __launch_bounds__(256) void block_chol_kernel(const double* __restric
     // the diagonal tile kb: its inverse factor into X
     auto diagonal = [&](int kb) {
         double a[16], x[4];
+        unsigned no = 0;
+        const double least = scaled ? 0.0 : inv[16 * kb + lc];
 #pragma unroll
         for (int j = 0; j < 16; ++j) a[j] = A[(16 * kb + lc) * LD + 16 * kb + j] + (j == lc ? shift : 0.0);
 #pragma unroll
         for (int m = 0; m < 4; ++m) x[m] = 4 * lr + m == lc ? 1.0 : 0.0;
-        diag_columns(a, x, lc, bad, std::make_integer_sequence<int, 16>());
+        diag_columns(a, x, lc, least, drop, no, std::make_integer_sequence<int, 16>());
+        bad = bad || no;
+        if (lane == 0) gone_of[kb] = drop ? no : 0;
 #pragma unroll
         for (int m = 0; m < 4; ++m) X[(16 * kb + lc) * LD + 16 * kb + 4 * lr + m] = x[m];
     };
@@ -598,8 +619,10 @@ __global__ __launch_bounds__(256) void block_chol_kernel(const double* __restric
             const int r = 16 * p + ty, c = 16 * q + tx;
             if (r >= b || c >= b) continue;
             const double f = scaled ? inv[r] : 1.0;
-            Rinv[r * b + c] = X[c * LD + r] * (f != 0.0 ? f : 1.0);
+            const bool unit = r == c && (gone_of[q] >> tx & 1);
+            Rinv[r * b + c] = unit ? 1.0 : X[c * LD + r] * (f != 0.0 ? f : 1.0);
         }
+    if (drop && tid < b) tiny[tid] = gone_of[tid / 16] >> (tid % 16) & 1;
 }
 
 // calls f with the number of 16-column tiles as a compile-time constant

@@ -58,8 +58,10 @@ int block_reduce(double* part, i64 p_bs, const int* skip, const BlockCut& q, hip
 // S + shift_rel tr(S) I, S the sum of np partials.  scaled: S is first scaled to a unit diagonal, D^{-1} S D^{-1},
 // and D^{-1} R^{-1} returned; columns of norm at most 1e-30 of the largest count as absent (tiny[k] = 1, unit
 // row and column in S).  near (not null): near[i] = 1 if S_i (scaled, and no column absent) is within near_tol of the
-// identity in the Frobenius norm, and then there is no shift.  flag |= 2 on a non-positive pivot.  Instances
-// with skip[i] != 0 are left as they are, with near[i] = 1.
+// identity in the Frobenius norm, and then there is no shift.  Not scaled, with tiny given: columns that depend
+// on the ones before them (a pivot within rounding of zero) are dropped, with tiny[k] = 1 (0 elsewhere) and column k
+// of R^{-1} the unit vector, for block_mult to put noise there.  flag |= 2 on such a pivot, or a non-positive one.
+// Instances with skip[i] != 0 are left as they are, with near[i] = 1.
 void block_chol(const double* part, i64 p_bs, int np, int b, int nb, double shift_rel, bool scaled, double* Rinv,
                 i64 r_bs, int* flag, const int* skip, int* near, double near_tol, int* tiny, i64 t_bs, hipStream_t s);
 

@@ -557,7 +557,8 @@ void persist_tuning(dtrg_plan* P) {
 // noise-level eigenvalues), and a plain pass follows.  The third pass is skipped when the second finds its
 // input within kOrthNear of orthonormal, and left out where the block feeds a product without a Rayleigh-Ritz
 // solve (ritz false): a block that is off by the first pass's rounding spans the same space.  Passes are
-// skipped on the device, per instance.  noise: columns that vanished are replaced by hash noise of that seed.
+// skipped on the device, per instance.  noise: columns that vanished, or that the passes after the first find to
+// depend on the ones before them, are replaced by hash noise of that seed.
 constexpr double kOrthFair = 0.5, kOrthNear = 1e-4;
 void orthonormalise_parts(Ctx& c, const BlockCut& q, const double* Y, const double* V, const BlockShift& sh,
                           const uint64_t* noise, bool ritz) {
@@ -573,17 +574,20 @@ void orthonormalise_parts(Ctx& c, const BlockCut& q, const double* Y, const doub
     block_mult(Y, V, sh, P->Rinv.p, P->Rinv.bs, noise ? P->tiny.p : nullptr, tbs, noise ? *noise : 0, P->V2.p,
                P->blkP.p, pbs, nullptr, first, q, c.s);
     std::swap(P->V1, P->V2);
+    // the passes after it replace, with noise, columns that turn out to depend on the ones before them
+    int* tiny = noise ? P->tiny.p : nullptr;
+    const uint64_t seed = noise ? *noise : 0;
     np = block_reduce(P->blkP.p, pbs, first, q, c.s);
     block_chol(P->blkP.p, pbs, np, b, nb, 0.0, false, P->Rinv.p, P->Rinv.bs, P->flags.p, first, second, kOrthNear,
-               nullptr, 0, c.s);
-    block_mult(P->V1.p, nullptr, {}, P->Rinv.p, P->Rinv.bs, nullptr, 0, 0, P->V1.p, ritz ? P->blkP.p : nullptr, pbs,
-               first, second, q, c.s);
+               tiny, tbs, c.s);
+    block_mult(P->V1.p, nullptr, {}, P->Rinv.p, P->Rinv.bs, tiny, tbs, seed + 1, P->V1.p, ritz ? P->blkP.p : nullptr,
+               pbs, first, second, q, c.s);
     if (!ritz) return;
     np = block_reduce(P->blkP.p, pbs, second, q, c.s);
-    block_chol(P->blkP.p, pbs, np, b, nb, 0.0, false, P->Rinv.p, P->Rinv.bs, P->flags.p, second, nullptr, 0.0, nullptr,
-               0, c.s);
-    block_mult(P->V1.p, nullptr, {}, P->Rinv.p, P->Rinv.bs, nullptr, 0, 0, P->V1.p, nullptr, pbs, second, nullptr, q,
-               c.s);
+    block_chol(P->blkP.p, pbs, np, b, nb, 0.0, false, P->Rinv.p, P->Rinv.bs, P->flags.p, second, nullptr, 0.0, tiny,
+               tbs, c.s);
+    block_mult(P->V1.p, nullptr, {}, P->Rinv.p, P->Rinv.bs, tiny, tbs, seed + 2, P->V1.p, nullptr, pbs, second, nullptr,
+               q, c.s);
 }
 
 // the n x b block X (V1, or Y1 where noise may be needed) orthonormalised into V1

@@ -187,7 +187,9 @@ typedef struct {
                                  above 1e-8 of the largest, for every instance), where the product of
                                  a block that is not aligned with eigenvectors loses no direction to
                                  rounding (each new block is still re-orthonormalised); after every
-                                 product before that, and with 0.  The first solve of a step counts
+                                 product before that, and with 0.  (Eigenpairs that are found block by
+                                 block: also only where every value of the block is above 1e-11 of
+                                 the Gram's trace.)  The first solve of a step counts
                                  only for scheme (a) and a start from the previous step's vectors.
                                  The iteration still ends on a solve, whose Ritz residuals decide
                                  convergence.  The choice is made in the adaptive pass and replayed.

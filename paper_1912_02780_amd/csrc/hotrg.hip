@@ -124,6 +124,12 @@ constexpr double kSubspaceAccept = 1e-12;   // largest accepted resolved residua
 // Rayleigh-Ritz after every (rr_skip + 1)-th Gram product only where the Ritz values of a solve span less than
 // this ratio (smallest over largest, every instance)
 constexpr double kRrSkipRatio = 1e-8;
+// ... and, in the blocks of a block-locked solve, only where they are above this (absolute, on the trace-normalised
+// Gram).  A block that starts far down the spectrum can have values within eight decades of each other and all of
+// them rounding.  A product is wrong by u = 2^-53 of the Gram's norm, not of the block's values, and brings the
+// locked vectors back at the ratio u / (0.04 theta) (0.04 theta: what the first Chebyshev zero leaves of the smallest
+// value), which the single deflation between two solves has to keep small: 3e-4 here.
+constexpr double kRrSkipFloor = 1e-11;
 constexpr double kChebTail = 1e-15;         // relative size of the last two expansion coefficients
 constexpr int kChebMaxDegree = 1024;
 // at the largest degree the expansion is accepted down to this tail (a relative error of the
@@ -740,14 +746,15 @@ struct RitzPlan {
         return stride == 1 && P->opt.rr_skip && !(it == 1 && (!warm || P->chain()));
     }
     // After that solve, with its Ritz values: take the stride up where they allow it.
-    void decide(const dtrg_plan* P, int it, const std::vector<double>& th, int b) {
-        double ratio = INFINITY;
+    void decide(const dtrg_plan* P, int it, const std::vector<double>& th, int b, double floor) {
+        double ratio = INFINITY, least = INFINITY;
         for (int i = 0; i < P->nb; ++i) {
             const double* t = th.data() + (size_t)i * P->th.bs;
             ratio = std::min(ratio, t[0] > 0.0 ? t[b - 1] / t[0] : 0.0);
+            least = std::min(least, t[b - 1]);
         }
         from = it;
-        if (ratio > kRrSkipRatio) stride = 1 + P->opt.rr_skip;
+        if (ratio > kRrSkipRatio && least > floor) stride = 1 + P->opt.rr_skip;
     }
 };
 
@@ -815,7 +822,7 @@ void eigensolve_locked(Ctx& c, StepCk& st, int k, const StepCk* warm) {
             if (stall >= 3 && mx <= kSubspaceAccept) break;      // rounding floor reached
             if (it == it_max) break;
             // next block: (G + s I) V, deflated and re-orthonormalised
-            if (rr.open(P, it, warm_used)) rr.decide(P, it, thh, bw);
+            if (rr.open(P, it, warm_used)) rr.decide(P, it, thh, bw, kRrSkipFloor);
             axpy(P->V1.p, P->Y1.p, vbs, (i64)n * bw, nb, kChainGramShift, c.s);
             deflate(c, st.U.p, b, ubs, c0, P->Y1.p, bw, vbs, n);
             orthonormalise(c, P->Y1.p, n, bw, &noise);
@@ -914,7 +921,7 @@ void eigensolve(Ctx& c, StepCk& st, int k, const StepCk* warm) {
             if (mx > 0.5 * prev) ++stall; else stall = 0;
             prev = mx;
             if (stall >= 3 && mx <= kSubspaceAccept) break;      // rounding floor reached
-            if (rr.open(P, it, warm_used)) rr.decide(P, it, thh, b);
+            if (rr.open(P, it, warm_used)) rr.decide(P, it, thh, b, 0.0);
         }
         if (it == it_max) break;
         orthonormalise_parts(c, q, P->Y1.p, shifted ? P->V1.p : nullptr, sh, &noise, rr.solve(it + 1, it_max));

@@ -726,9 +726,10 @@ void rayleigh_ritz(Ctx& c, const BlockCut& q, const double* W, const BlockShift*
 struct RitzPlan {
     int stride = 1, from = 0;
     bool solve(int it, int it_max) const { return it <= from || (it - from) % stride == 0 || it == it_max; }
-    // the shift of the block built after product `it`; `shifted` false: G V itself
-    BlockShift shift(const dtrg_plan* P, int it, bool& shifted) const {
-        const bool zeros = stride > 1 && it > from && P->opt.subspace_shift;
+    // the shift of the block built after product `it`; `shifted` false: G V itself.  decided: the stride was
+    // known before that block was begun, also if this is the solve that took it up.
+    BlockShift shift(const dtrg_plan* P, int it, bool& shifted, bool decided = false) const {
+        const bool zeros = stride > 1 && (it > from || (it == from && decided)) && P->opt.subspace_shift;
         shifted = P->chain() || P->opt.subspace_shift;
         BlockShift sh;
         if (P->chain() && !zeros) {
@@ -823,7 +824,9 @@ void eigensolve_locked(Ctx& c, StepCk& st, int k, const StepCk* warm) {
             if (it == it_max) break;
             // next block: (G + s I) V, deflated and re-orthonormalised
             if (rr.open(P, it, warm_used)) rr.decide(P, it, thh, bw, kRrSkipFloor);
-            axpy(P->V1.p, P->Y1.p, vbs, (i64)n * bw, nb, kChainGramShift, c.s);
+            const BlockShift sh = rr.shift(P, it, shifted, true);
+            if (sh.theta) axpy(P->V1.p, P->Y1.p, vbs, (i64)n * bw, nb, -sh.f, c.s, sh.theta + bw - 1, sh.th_bs);
+            else axpy(P->V1.p, P->Y1.p, vbs, (i64)n * bw, nb, sh.c, c.s);
             deflate(c, st.U.p, b, ubs, c0, P->Y1.p, bw, vbs, n);
             orthonormalise(c, P->Y1.p, n, bw, &noise);
         }

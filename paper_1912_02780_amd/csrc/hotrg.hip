@@ -596,12 +596,12 @@ void orthonormalise_parts(Ctx& c, const BlockCut& q, const double* Y, const doub
                q, c.s);
 }
 
-// the n x b block X (V1, or Y1 where noise may be needed) orthonormalised into V1
-void orthonormalise(Ctx& c, double* X, int n, int b, const uint64_t* noise = nullptr) {
+// the n x b block X (V1 or Y1) orthonormalised into V1
+void orthonormalise(Ctx& c, double* X, int n, int b) {
     dtrg_plan* P = c.P;
     const BlockCut q = block_cut(n, b, P->nb, P->V1.bs);
     block_gram(X, nullptr, nullptr, 0, {}, P->blkP.p, P->blkP.bs, q, c.s);
-    orthonormalise_parts(c, q, X, nullptr, {}, noise, true);
+    orthonormalise_parts(c, q, X, nullptr, {}, nullptr, true);
 }
 
 // C (n x b) = G (n x n) V (n x b)
@@ -765,6 +765,9 @@ struct RitzPlan {
 // blocks before it resolved (they are eigenvectors of the Gram, so the deflated Gram has the
 // remaining spectrum).  Each block resolves lock_r pairs to the tolerance; the last block's guard
 // columns complete U, its first unresolved pair bounds the complement of the eigen-adjoint.
+// No column of a new block is replaced by noise, which would have to be deflated too: none vanishes.  (G + s I) v of
+// a unit vector in the locked vectors' complement has norm s = 2^-45 or more, and between solves (G - s I) v has
+// 0.04 theta_{b-1} or more, above 4e-13 (kRrSkipFloor), since s lies below every Ritz value of the block.
 // Adaptive passes only (scheme (b) plans are not batched).
 void eigensolve_locked(Ctx& c, StepCk& st, int k, const StepCk* warm) {
     dtrg_plan* P = c.P;
@@ -794,7 +797,6 @@ void eigensolve_locked(Ctx& c, StepCk& st, int k, const StepCk* warm) {
         RitzPlan rr;
         rr.from = it_max;
         for (it = 1; it <= it_max; ++it) {
-            const uint64_t noise = seed + 7919ULL * it + 104729ULL * (uint64_t)blk;
             bool shifted = false;
             product_G(c, st, k, P->V1.p, P->Y1.p, vbs, bw);
             if (!rr.solve(it, it_max)) {
@@ -802,7 +804,7 @@ void eigensolve_locked(Ctx& c, StepCk& st, int k, const StepCk* warm) {
                 const BlockShift sh = rr.shift(P, it, shifted);
                 deflate(c, st.U.p, b, ubs, c0, P->Y1.p, bw, vbs, n, 1);
                 block_gram(P->Y1.p, P->V1.p, nullptr, 0, sh, P->blkP.p, P->blkP.bs, q, c.s);
-                orthonormalise_parts(c, q, P->Y1.p, nullptr, {}, &noise, rr.solve(it + 1, it_max));
+                orthonormalise_parts(c, q, P->Y1.p, nullptr, {}, nullptr, rr.solve(it + 1, it_max));
                 continue;
             }
             deflate(c, st.U.p, b, ubs, c0, P->Y1.p, bw, vbs, n);
@@ -828,7 +830,7 @@ void eigensolve_locked(Ctx& c, StepCk& st, int k, const StepCk* warm) {
             if (sh.theta) axpy(P->V1.p, P->Y1.p, vbs, (i64)n * bw, nb, -sh.f, c.s, sh.theta + bw - 1, sh.th_bs);
             else axpy(P->V1.p, P->Y1.p, vbs, (i64)n * bw, nb, sh.c, c.s);
             deflate(c, st.U.p, b, ubs, c0, P->Y1.p, bw, vbs, n);
-            orthonormalise(c, P->Y1.p, n, bw, &noise);
+            orthonormalise(c, P->Y1.p, n, bw);
         }
         total += std::min(it, it_max);
         // lock the resolved pairs (and, for the last block, its guard) into U and lam

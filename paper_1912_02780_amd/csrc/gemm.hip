@@ -98,78 +98,94 @@ i64 gemm_c_extent(const GemmOp& op) {
 
 namespace {
 // Estimated time (us) of an FP64 or FP32 contraction on tile 1 (64 x 64) or 2 (128 x 128) with K in `splits`
-// chunks.  The matrix cores set the rate once a compute unit has two (four) blocks; what the choice turns on
-// is the number of blocks the busiest of the 256 units gets, a lone 64 x 64 block being bound by the latency
-// of its loads, and the pass over the partials.  Measured against the larger tile and a fixed split that it
-// replaces (FP64, us): 13824 x 576 x 576 199 against 248 (64 x 64: 8 rounds of small tiles for 3 of large
-// ones), 4096 x 256 x 256 24 against 39, 576^3 25 against 35, 2304 x 2304 x 110592 19.6e3 against 23.9e3
-// (3 chunks, 972 blocks, against 4, 1296: the last wave of blocks nearly full); and it keeps 128 x 128 where that is
-// faster: 32768 x 1024 x 1024 1114 against 1342, 2304^3 473 against 556.
+// chunks: a launch, the K steps (16) of the blocks that the busiest compute unit gets, and the pass over the partials.
+// A unit runs four (two) blocks at a time, and a step of r of them takes c + r s: the latency of loads,
+// LDS and barrier once, the matrix cores for each.  Which unit is the busiest follows from the order of the tiles:
+// an XCD (32 units) has an eighth of them, rounded up, in every chunk, so that 62 chunks of one tile are 62 blocks
+// on one XCD, two to a unit, and not 62 on 256.
+// The numbers are a fit to 420 random outputs (16 to 40000 x 16 to 8192, K 16 to 40000, every layout, up to 64
+// chunks); on those and 160 others, 7000 runs a type, it is 6% off in FP64 and 8% in FP32 (mean).
 double tile_time(Prec prec, const GemmOp& op, int tile, int splits) {
     int k_chunk = 0, s = 1;
     GemmCfg c;
     c.tile = tile;
     c.splits = splits;
     resolve_chunks(prec, op, c, k_chunk, s);
-    const double nz = (double)op.batch * op.batch2;
-    const double blocks = (double)tile_count(op, tile_rows(tile), tile_cols(tile)) * nz * s;
-    const i64 n = (i64)((blocks + 255) / 256);   // blocks of the busiest unit
+    const i64 nz = (i64)op.batch * op.batch2;
+    const i64 tiles = (tile_count(op, tile_rows(tile), tile_cols(tile)) + kXcds - 1) / kXcds;
+    const i64 n = (tiles * nz * s + 31) / 32;   // blocks of the busiest unit
     const double steps = (double)(k_chunk / bk_of(prec, tile));
-    // a K step of one 128 x 128 block on a unit of its own (64 x 64: a quarter, but not below the latency), and
-    // the rate of each tile relative to it
-    const double one = prec == Prec::F64 ? 1.7 : 0.85, latency = 0.9;
+    struct Cost { double launch, wait, step; };
+    const Cost f64[2] = {{5.8, 0.62, 0.52}, {6.9, 0.44, 1.94}}, f32[2] = {{6.1, 0.44, 0.29}, {7.8, 0.46, 1.17}};
+    const Cost q = (prec == Prec::F64 ? f64 : f32)[tile - 1];
     const int full = tile == 2 ? 2 : 4;
-    const double step = tile == 2 ? one : 0.25 * one;
     const i64 rest = n % full;
-    double t = steps * ((double)(n / full) * full * step + (rest ? std::max(step * (double)rest, latency) : 0.0)) /
-               (tile == 2 ? 0.95 : 0.82);
-    if (s > 1) t += 4.0 + (s + 1) * (double)op.M * op.N * nz * (prec == Prec::F64 ? 8.0 : 4.0) / 3.0e6;
+    double t = q.launch + steps * ((double)(n / full) * (q.wait + full * q.step) + (rest ? q.wait + rest * q.step : 0.0));
+    const double out = (double)op.M * op.N * nz;
+    if (s > 1) t += prec == Prec::F64 ? 1.9 + (s + 1) * out * 8.0 / 3.9e6 : 2.8 + (s + 1) * out * 4.0 / 3.2e6;
     return t;
 }
 
 // the largest split-K workspace (bytes) the choice may spend: that of 1024 blocks of 128 x 128 in FP64
 constexpr i64 kMaxSplitBytes = 128LL << 20;
+// Another tile and count than the fixed rule's are taken where the estimate gives them this much of its time, which
+// a wide output, where it is more accurate, may come closer to.  Over the 580 outputs the choice takes 0.871 (FP64)
+// and 0.883 (FP32) of the rule's time, geometric mean (0.867 and 0.881 with no margin), and is more than 3%
+// slower on 14 and 11 of them (30 and 50), at most by 18%.
+constexpr double kChoiceMargin = 0.85, kChoiceMarginWide = 0.9;
 }  // namespace
 
 GemmCfg gemm_resolve(Prec prec, const GemmOp& op) {
     GemmCfg c = op.cfg;
     const bool split = prec_planes(prec) > 1;
     if (!split && c.tile <= 2 && (c.tile == 0 || c.splits <= 0)) {
-        // FP64 and FP32: the tile and split count (those not given) of the least estimated time
-        int floor = gemm_chain_splits(prec, op);
-        if (prec == Prec::F32) {
-            // The length of an FP32 chain sets its rounding, so that the estimate only chooses among splits that
-            // leave chains no longer than filling the chip several times over (1024 blocks) would, or than 1024
-            // products where the partials fit: gradients with FP32 contractions at chi = 35 and 24 are then
-            // 1.0e-6 and 5.7e-7 off FP64 (mean of 8 random tensors; 1.06e-6 with the first limit alone), and
-            // 1225 x 1225 x 42875 takes 1.56 ms either way.
-            const bool big = (op.M >= 256 && op.N >= 128) || (op.N >= 256 && op.M >= 128);
-            const int t = op.cfg.tile != 0 ? op.cfg.tile : (big ? 2 : 1);
-            const i64 tiles = tile_count(op, tile_rows(t), tile_cols(t)) * op.batch * op.batch2;
-            if (tiles < 512)
-                floor = (int)std::max<i64>(floor, std::min<i64>({(1024 + tiles - 1) / tiles,
-                                                                std::max<i64>(1, op.K / (bk_of(prec, t) * 8)), 64}));
-            const i64 bytes = std::max<i64>(1, (i64)op.batch * op.batch2 * op.M * op.N * 4);
-            floor = (int)std::max<i64>(floor, std::min<i64>({(op.K + 1023) / 1024, kMaxSplitBytes / bytes, 64,
-                                                            65535 / ((i64)op.batch * op.batch2)}));
-        }
-        const i64 part = std::max<i64>(1, (i64)op.batch * op.batch2 * op.M * op.N * (prec == Prec::F64 ? 8 : 4));
+        // FP64 and FP32: what is not given by a fixed rule, 128 x 128 for large outputs and enough chunks to fill
+        // the 256 compute units several times over where the output alone does not, or by estimated time where that
+        // is clearly less.  13824 x 576 x 576 takes 199 us on 64 x 64 and 248 on 128 x 128 (FP64), 4096 x 256 x 256
+        // 24 against 39, 576^3 25 against 35, 2304 x 2304 x 110592 19.6e3 in 3 chunks against 23.9e3 in 4.
         const i64 nz = (i64)op.batch * op.batch2;
-        double best = -1.0;
+        const bool big = (op.M >= 256 && op.N >= 128) || (op.N >= 256 && op.M >= 128);
         GemmCfg pick = c;
+        if (pick.tile == 0) pick.tile = big ? 2 : 1;
+        const i64 tiles = std::max<i64>(1, tile_count(op, tile_rows(pick.tile), tile_cols(pick.tile)) * nz);
+        const i64 part = std::max<i64>(1, nz * op.M * op.N * (prec == Prec::F64 ? 8 : 4));
+        int fill = 1, least = gemm_chain_splits(prec, op);
+        if (tiles < 512)
+            fill = (int)std::min<i64>({(1024 + tiles - 1) / tiles, std::max<i64>(1, op.K / (bk_of(prec, pick.tile) * 8)), 64});
+        if (prec == Prec::F32) {
+            // The length of an FP32 chain sets its rounding: chains are never longer than the rule makes them, and
+            // where the output does not fill the chip anyway no longer than 1024 products as far as the
+            // partials fit (gradients with FP32 contractions at chi = 35 and 24 are then 1.0e-6 and 5.7e-7 off FP64,
+            // mean of 8 random tensors; 1.06e-6 without).  An output that fills it is not split for that:
+            // 4096 x 4096 x 2048 took 740 us in two chunks and takes 698, 8192 x 2048 x 1536 576 and 522.
+            least = std::max(least, fill);
+            if (tiles < 512)
+                least = (int)std::max<i64>(least, std::min<i64>({(op.K + 1023) / 1024, kMaxSplitBytes / part, 64, 65535 / nz}));
+        }
+        if (pick.splits <= 0) pick.splits = std::max(fill, least);
+        const double base = tile_time(prec, op, pick.tile, pick.splits);
+        double best = (std::min(op.M, op.N) >= 256 ? kChoiceMarginWide : kChoiceMargin) * base;
         for (int tile = 1; tile <= 2; ++tile) {
             if (op.cfg.tile != 0 && op.cfg.tile != tile) continue;
             const i64 most = std::min<i64>({64, op.K / (bk_of(prec, tile) * 4), kMaxSplitBytes / part, 65535 / nz});
-            const int lo = op.cfg.splits > 0 ? op.cfg.splits : floor;
-            const int hi = op.cfg.splits > 0 ? op.cfg.splits : (int)std::max<i64>(floor, most);
+            const int lo = op.cfg.splits > 0 ? op.cfg.splits : least;
+            const int hi = op.cfg.splits > 0 ? op.cfg.splits : (int)std::max<i64>(least, most);
             for (int s = lo; s <= hi; s += 1 + s / 8) {
                 const double t = tile_time(prec, op, tile, s);
-                if (best < 0.0 || t < best) {
+                if (t < best) {
                     best = t;
                     pick.tile = tile;
                     pick.splits = s;
                 }
             }
+        }
+        if (prec == Prec::F32 && op.cfg.splits <= 0 && tiles < 512 && op.K <= 1024) {
+            // the shortest chains that cost no more than 5%: chi = 16 gradients are 4.1e-7 off FP64 with chains of
+            // 64 and 5.3e-7 with 128, which 4096 x 256 x 256 would take otherwise, in the same time
+            const i64 most = std::min<i64>({64, op.K / (bk_of(prec, pick.tile) * 4), kMaxSplitBytes / part, 65535 / nz});
+            const double limit = 1.05 * tile_time(prec, op, pick.tile, pick.splits);
+            for (int s = pick.splits; s <= most; s += 1 + s / 8)
+                if (tile_time(prec, op, pick.tile, s) <= limit) pick.splits = s;
         }
         return pick;
     }

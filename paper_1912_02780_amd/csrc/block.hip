@@ -25,6 +25,7 @@ __device__ inline v4d mma(double a, double b, v4d c) { return __builtin_amdgcn_m
 constexpr int kMaxTiles = 6;          // b <= 96
 constexpr int kConsumerParts = 8;     // partials a single workgroup adds up itself
 constexpr int kMaxSplits = 8;         // parts of a product's inner index
+constexpr double kDropped = -1.0;     // in place of a diagonal entry of R^{-1} (positive): noise for this column
 
 __device__ inline double shift_of(const BlockShift& sh, int z, int b) {
     return sh.theta ? -sh.f * sh.theta[z * sh.th_bs + b - 1] : sh.c;
@@ -35,6 +36,12 @@ __device__ inline uint64_t mix64(uint64_t z) {
     z = (z ^ (z >> 30)) * 0xbf58476d1ce4e5b9ULL;
     z = (z ^ (z >> 27)) * 0x94d049bb133111ebULL;
     return z ^ (z >> 31);
+}
+
+// hash noise of element `at` of a block, uniform in (-unit, unit)
+__device__ inline double noise_of(uint64_t seed, i64 at, double unit) {
+    const uint64_t h = mix64(seed ^ mix64((uint64_t)at));
+    return ((double)(h >> 11) * (2.0 / 9007199254740992.0) - 1.0) * unit;
 }
 
 // Where a lane sits: lr = lane / 16, lc = lane mod 16, column tile w.
@@ -305,7 +312,8 @@ __global__ __launch_bounds__(128) void block_residual_kernel(const double* __res
 template <int T>
 __global__ __launch_bounds__(64 * T) void block_mult_kernel(const double* X, const double* V, i64 vbs,
                                                             BlockShift shift, const double* __restrict__ R, i64 r_bs,
-                                                            const int* __restrict__ tiny, i64 t_bs, uint64_t seed,
+                                                            const int* __restrict__ tiny, i64 t_bs, int drop,
+                                                            uint64_t seed,
                                                             double* Out, double* __restrict__ part, i64 p_bs,
                                                             const int* __restrict__ skip,
                                                             const int* __restrict__ nogram, int n, int b, int rows) {
@@ -339,6 +347,14 @@ __global__ __launch_bounds__(64 * T) void block_mult_kernel(const double* X, con
         for (int k = 0; k < 4 * T; ++k) noise |= (unsigned)(t[k] != 0 && 4 * k + L.lr < b) << k;
     }
     const bool noisy = __ballot(noise != 0) != 0;
+    // a dropped column: its mark is with the lane that has the diagonal entry (row 4 k + lr, lr = lc mod 4)
+    bool fill = false;
+    if (drop) {
+        bool mark = false;
+#pragma unroll
+        for (int k = 0; k < 4 * T; ++k) mark |= 4 * k + L.lr == L.col && rf[k] == kDropped;
+        fill = (__ballot(mark) & (0x0001000100010001ULL << L.lc)) != 0;
+    }
     v4d acc[T];
 #pragma unroll
     for (int i = 0; i < T; ++i) acc[i] = v4d{0, 0, 0, 0};
@@ -366,8 +382,7 @@ __global__ __launch_bounds__(64 * T) void block_mult_kernel(const double* X, con
 #pragma unroll
             for (int k = 0; k < 4 * T; ++k)
                 if (noise >> k & 1) {
-                    const uint64_t h = mix64(seed ^ mix64((uint64_t)(at + 4 * k + L.lr)));
-                    a[k] = ((double)(h >> 11) * (2.0 / 9007199254740992.0) - 1.0) * unit;
+                    a[k] = noise_of(seed, at + 4 * k + L.lr, unit);
                 }
         }
         v4d p0 = {0, 0, 0, 0}, p1 = {0, 0, 0, 0};
@@ -384,6 +399,10 @@ __global__ __launch_bounds__(64 * T) void block_mult_kernel(const double* X, con
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
             x[r] = p0[r] + p1[r];
+            if (fill) {
+                const int ro = rb + L.lr + 4 * r;
+                x[r] = ro < r1 ? noise_of(seed, (i64)ro * b + L.col, unit) : 0.0;
+            }
             if (gram) sh[buf][L.w][r][L.lane] = x[r];
         }
         __syncthreads();
@@ -427,10 +446,10 @@ __global__ __launch_bounds__(256) void block_reduce_kernel(double* part, i64 p_b
 // A Gram of numerically low rank (the Ising model deep in a phase) gives blocks of fewer directions than columns.
 // The shift carries the first pass over that; in the plain passes after it a column that depends on the ones
 // before it has a pivot that is rounding only, of either sign, and its reciprocal root would fill the tiles
-// after it with infinities.  Where the caller can replace columns (tiny), such a column is dropped instead: its row
-// of L^{-1} and its column of L are zero, and the block gets hash noise in its place, which the next pass
-// orthonormalises.  kDependent: that far below the column's squared norm the pivot is rounding (96 columns:
-// 2^-53 x 96 = 2^-46.4, and the explicit inverses of the tiles add to it).
+// after it with infinities.  Where the caller asks for it, such a column is dropped instead: its row of L^{-1} and
+// its column of L are zero but for the mark kDropped on the diagonal, and block_mult puts hash noise in its place,
+// which the next pass orthonormalises.  kDependent: that far below the column's squared norm the pivot is rounding (96
+// columns: 2^-53 x 96 = 2^-46.4, and the explicit inverses of the tiles add to it).
 constexpr double kDependent = 0x1p-42;
 
 __device__ inline double rsqrt64(double d) {
@@ -449,14 +468,14 @@ __device__ inline double row_bcast(double v) {   // the value of lane J of this 
 }
 
 // column K of a 16 x 16 tile: row i = lane mod 16 in a, columns 4 (lane / 16) + m of the inverse in x.  Bit K of bad:
-// its pivot is not above `least` (of row i, 0 unless columns are dropped) or not finite.
-template <int K, int... J>
-__device__ inline void diag_column(double (&a)[16], double (&x)[4], int i, double least, bool drop, unsigned& bad,
+// its pivot is not positive (DROP: above `least` of row K) or not finite.
+template <bool DROP, int K, int... J>
+__device__ inline void diag_column(double (&a)[16], double (&x)[4], int i, double least, unsigned& bad,
                                    std::integer_sequence<int, J...>) {
     double d = row_bcast<K>(a[K]);
-    const bool no = !(d > row_bcast<K>(least)) || !isfinite(d);
+    const bool no = !(d > (DROP ? row_bcast<K>(least) : 0.0)) || !isfinite(d);
     if (no) { bad |= 1u << K; d = 1e-300; }
-    const double r = no && drop ? 0.0 : rsqrt64(d);
+    const double r = DROP && no ? 0.0 : rsqrt64(d);
     const double l = i > K ? a[K] * r : 0.0;
     ((a[K + 1 + J] -= l * row_bcast<K + 1 + J>(l)), ...);
 #pragma unroll
@@ -465,13 +484,14 @@ __device__ inline void diag_column(double (&a)[16], double (&x)[4], int i, doubl
         x[m] = i == K ? xk : x[m] - l * xk;
     }
 }
-template <int... K>
-__device__ inline void diag_columns(double (&a)[16], double (&x)[4], int i, double least, bool drop, unsigned& bad,
+template <bool DROP, int... K>
+__device__ inline void diag_columns(double (&a)[16], double (&x)[4], int i, double least, unsigned& bad,
                                     std::integer_sequence<int, K...>) {
-    (diag_column<K>(a, x, i, least, drop, bad, std::make_integer_sequence<int, 15 - K>()), ...);
+    (diag_column<DROP, K>(a, x, i, least, bad, std::make_integer_sequence<int, 15 - K>()), ...);
 }
 
-template <int T>
+// DROP: not scaled, and dependent columns are dropped
+template <int T, bool DROP>
 __global__ __launch_bounds__(256) void block_chol_kernel(const double* __restrict__ part, i64 p_bs, int np, int b,
                                                          double shift, int scaled, double* __restrict__ Rinv,
                                                          i64 r_bs, int* flag, const int* skip, int* near,
@@ -479,8 +499,8 @@ __global__ __launch_bounds__(256) void block_chol_kernel(const double* __restric
     // rows 4 modulo 32 doubles apart: the 16 rows x 4 columns of an operand read fall on different banks
     constexpr int N = 16 * T, LD = N <= 36 ? 36 : (N <= 68 ? 68 : 100);
     __shared__ double A[N * LD], X[N * LD];
-    __shared__ double inv[N], dist[4];   // inv, not scaled: the least pivots
-    __shared__ unsigned gone_of[T];      // columns of a diagonal tile that were dropped
+    __shared__ double inv[N], dist[4];   // inv, DROP: the least pivots
+    __shared__ unsigned gone_of[T];      // DROP: the dropped columns of each diagonal tile
     const int tid = threadIdx.x, z = blockIdx.x, lane = tid & 63, w = tid >> 6, lr = lane >> 4, lc = lane & 15;
     const int ty = tid >> 4, tx = tid & 15;
     if (skip && skip[z]) {
@@ -490,7 +510,6 @@ __global__ __launch_bounds__(256) void block_chol_kernel(const double* __restric
     part += z * p_bs;
     Rinv += z * r_bs;
     if (tiny) tiny += z * t_bs;
-    const bool drop = tiny && !scaled;
     const int bb = b * b;
     auto sum = [&](int i) {
         double v[kConsumerParts], s = 0.0;
@@ -533,7 +552,7 @@ __global__ __launch_bounds__(256) void block_chol_kernel(const double* __restric
             }
             const double e = v - (r == c ? 1.0 : 0.0);
             far += e * e;
-            if (r == c && !scaled) inv[r] = drop ? kDependent * v : 0.0;
+            if (DROP && r == c) inv[r] = kDependent * v;
             A[r * LD + c] = v;
             X[r * LD + c] = 0.0;
         }
@@ -548,14 +567,14 @@ __global__ __launch_bounds__(256) void block_chol_kernel(const double* __restric
     auto diagonal = [&](int kb) {
         double a[16], x[4];
         unsigned no = 0;
-        const double least = scaled ? 0.0 : inv[16 * kb + lc];
+        const double least = DROP ? inv[16 * kb + lc] : 0.0;
 #pragma unroll
         for (int j = 0; j < 16; ++j) a[j] = A[(16 * kb + lc) * LD + 16 * kb + j] + (j == lc ? shift : 0.0);
 #pragma unroll
         for (int m = 0; m < 4; ++m) x[m] = 4 * lr + m == lc ? 1.0 : 0.0;
-        diag_columns(a, x, lc, least, drop, no, std::make_integer_sequence<int, 16>());
+        diag_columns<DROP>(a, x, lc, least, no, std::make_integer_sequence<int, 16>());
         bad = bad || no;
-        if (lane == 0) gone_of[kb] = drop ? no : 0;
+        if (DROP && lane == 0) gone_of[kb] = no;
 #pragma unroll
         for (int m = 0; m < 4; ++m) X[(16 * kb + lc) * LD + 16 * kb + 4 * lr + m] = x[m];
     };
@@ -619,10 +638,9 @@ __global__ __launch_bounds__(256) void block_chol_kernel(const double* __restric
             const int r = 16 * p + ty, c = 16 * q + tx;
             if (r >= b || c >= b) continue;
             const double f = scaled ? inv[r] : 1.0;
-            const bool unit = r == c && (gone_of[q] >> tx & 1);
-            Rinv[r * b + c] = unit ? 1.0 : X[c * LD + r] * (f != 0.0 ? f : 1.0);
+            const bool dropped = DROP && r == c && (gone_of[q] >> tx & 1);
+            Rinv[r * b + c] = dropped ? kDropped : X[c * LD + r] * (f != 0.0 ? f : 1.0);
         }
-    if (drop && tid < b) tiny[tid] = gone_of[tid / 16] >> (tid % 16) & 1;
 }
 
 // calls f with the number of 16-column tiles as a compile-time constant
@@ -711,12 +729,12 @@ void block_residuals(const double* rpart, i64 r_bs, double* res, i64 res_bs, con
 }
 
 void block_mult(const double* X, const double* V, const BlockShift& sh, const double* R, i64 r_bs, const int* tiny,
-                i64 t_bs, uint64_t seed, double* Out, double* part, i64 p_bs, const int* skip, const int* nogram,
-                const BlockCut& q, hipStream_t s) {
+                i64 t_bs, bool drop, uint64_t seed, double* Out, double* part, i64 p_bs, const int* skip,
+                const int* nogram, const BlockCut& q, hipStream_t s) {
     check_cut(q);
     with_tiles(q.b, [&](auto T) {
         hipLaunchKernelGGL((block_mult_kernel<T()>), dim3(q.chunks, q.nb), dim3(64 * T()), 0, s, X, V, q.vbs, sh, R,
-                           r_bs, tiny, t_bs, seed, Out, part, p_bs, skip, nogram, q.n, q.b, q.rows);
+                           r_bs, tiny, t_bs, drop ? 1 : 0, seed, Out, part, p_bs, skip, nogram, q.n, q.b, q.rows);
     });
     DTRG_HIP(hipGetLastError());
 }
@@ -731,15 +749,20 @@ int block_reduce(double* part, i64 p_bs, const int* skip, const BlockCut& q, hip
 }
 
 void block_chol(const double* part, i64 p_bs, int np, int b, int nb, double shift_rel, bool scaled, double* Rinv,
-                i64 r_bs, int* flag, const int* skip, int* near, double near_tol, int* tiny, i64 t_bs,
+                i64 r_bs, int* flag, const int* skip, int* near, double near_tol, int* tiny, i64 t_bs, bool drop,
                 hipStream_t s) {
     DTRG_REQUIRE(b >= 1 && b <= 16 * kMaxTiles && np >= 1 && np <= kConsumerParts, DTRG_EINVAL,
                  "block_chol: bad sizes");
-    DTRG_REQUIRE(scaled || shift_rel == 0.0, DTRG_EINVAL, "block_chol: a shift needs a scaled Gram");
+    DTRG_REQUIRE(scaled ? !drop : shift_rel == 0.0 && !tiny, DTRG_EINVAL,
+                 "block_chol: a shift and absent columns need a scaled Gram, dropped ones a plain one");
     const double shift = shift_rel * b;   // the trace of a unit diagonal
     with_tiles(b, [&](auto T) {
-        hipLaunchKernelGGL((block_chol_kernel<T()>), dim3(nb), dim3(256), 0, s, part, p_bs, np, b, shift,
-                           scaled ? 1 : 0, Rinv, r_bs, flag, skip, near, near_tol, tiny, t_bs);
+        auto go = [&](auto DROP) {
+            hipLaunchKernelGGL((block_chol_kernel<T(), DROP()>), dim3(nb), dim3(256), 0, s, part, p_bs, np, b, shift,
+                               scaled ? 1 : 0, Rinv, r_bs, flag, skip, near, near_tol, tiny, t_bs);
+        };
+        if (drop) go(std::true_type());
+        else go(std::false_type());
     });
     DTRG_HIP(hipGetLastError());
 }

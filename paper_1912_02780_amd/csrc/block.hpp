@@ -45,12 +45,13 @@ void block_residuals(const double* rpart, i64 r_bs, double* res, i64 res_bs, con
 void block_gram(double* X, const double* V, const double* W, i64 w_bs, const BlockShift& sh, double* part, i64 p_bs,
                 const BlockCut& q, hipStream_t s);
 // Out = X R (R b x b upper triangular); Out may be X.  V not null: X + c V in place of X.  Columns k with
-// tiny[k] != 0 (tiny not null) are replaced by hash noise of unit scale before the product.  part (not null):
+// tiny[k] != 0 (tiny not null) are replaced by hash noise of unit scale before the product, and with drop those
+// of Out that block_chol dropped after it.  part (not null):
 // partial Out^T Out, not formed for instances with nogram[i] != 0.  Instances with skip[i] != 0 are left as
 // they are.
 void block_mult(const double* X, const double* V, const BlockShift& sh, const double* R, i64 r_bs, const int* tiny,
-                i64 t_bs, uint64_t seed, double* Out, double* part, i64 p_bs, const int* skip, const int* nogram,
-                const BlockCut& q, hipStream_t s);
+                i64 t_bs, bool drop, uint64_t seed, double* Out, double* part, i64 p_bs, const int* skip,
+                const int* nogram, const BlockCut& q, hipStream_t s);
 // Sum the chunks of part into the first where there are more than a consumer adds up itself; returns how many
 // are left.  skip as in block_mult.
 int block_reduce(double* part, i64 p_bs, const int* skip, const BlockCut& q, hipStream_t s);
@@ -58,12 +59,12 @@ int block_reduce(double* part, i64 p_bs, const int* skip, const BlockCut& q, hip
 // S + shift_rel tr(S) I, S the sum of np partials.  scaled: S is first scaled to a unit diagonal, D^{-1} S D^{-1},
 // and D^{-1} R^{-1} returned; columns of norm at most 1e-30 of the largest count as absent (tiny[k] = 1, unit
 // row and column in S).  near (not null): near[i] = 1 if S_i (scaled, and no column absent) is within near_tol of the
-// identity in the Frobenius norm, and then there is no shift.  Not scaled, with tiny given: columns that depend
-// on the ones before them (a pivot within rounding of zero) are dropped, with tiny[k] = 1 (0 elsewhere) and column k
-// of R^{-1} the unit vector, for block_mult to put noise there.  flag |= 2 on such a pivot, or a non-positive one.
-// Instances with skip[i] != 0 are left as they are, with near[i] = 1.
+// identity in the Frobenius norm, and then there is no shift.  drop (not scaled): columns that depend on the ones
+// before them (a pivot within rounding of zero) are left out and marked for block_mult.  flag |= 2 on such a pivot, or a
+// non-positive one.  Instances with skip[i] != 0 are left as they are, with near[i] = 1.
 void block_chol(const double* part, i64 p_bs, int np, int b, int nb, double shift_rel, bool scaled, double* Rinv,
-                i64 r_bs, int* flag, const int* skip, int* near, double near_tol, int* tiny, i64 t_bs, hipStream_t s);
+                i64 r_bs, int* flag, const int* skip, int* near, double near_tol, int* tiny, i64 t_bs, bool drop,
+                hipStream_t s);
 
 // C = G V for the Gram in Kronecker form G[(a,c)][(b,d)] = sum_jk A[a][b][jk] B[c][d][jk] / s (kron.hip), V and C
 // X^2 x w with ld w; W holds up to 16 partial sums of C.  Only sizes that kron_product_fits.

@@ -574,26 +574,26 @@ void orthonormalise_parts(Ctx& c, const BlockCut& q, const double* Y, const doub
     const double rel = 11.0 * ((double)q.n * b + (double)b * (b + 1)) * std::ldexp(1.0, -53);
     int* first = P->orth.p;         // the first pass was enough
     int* second = P->orth.p + nb;   // the second was
+    const uint64_t seed = noise ? *noise : 0;
+    // Scheme (b) has no dependent columns: the shift of its blocks keeps the old block's columns at 2^-45 of the trace.
+    const bool drop = noise && !P->chain();
     int np = block_reduce(P->blkP.p, pbs, nullptr, q, c.s);
     block_chol(P->blkP.p, pbs, np, b, nb, rel, true, P->Rinv.p, P->Rinv.bs, P->flags.p, nullptr, first, kOrthFair,
-               P->tiny.p, tbs, c.s);
-    block_mult(Y, V, sh, P->Rinv.p, P->Rinv.bs, noise ? P->tiny.p : nullptr, tbs, noise ? *noise : 0, P->V2.p,
-               P->blkP.p, pbs, nullptr, first, q, c.s);
+               P->tiny.p, tbs, false, c.s);
+    block_mult(Y, V, sh, P->Rinv.p, P->Rinv.bs, noise ? P->tiny.p : nullptr, tbs, false, seed, P->V2.p, P->blkP.p, pbs,
+               nullptr, first, q, c.s);
     std::swap(P->V1, P->V2);
-    // the passes after it replace, with noise, columns that turn out to depend on the ones before them
-    int* tiny = noise ? P->tiny.p : nullptr;
-    const uint64_t seed = noise ? *noise : 0;
     np = block_reduce(P->blkP.p, pbs, first, q, c.s);
     block_chol(P->blkP.p, pbs, np, b, nb, 0.0, false, P->Rinv.p, P->Rinv.bs, P->flags.p, first, second, kOrthNear,
-               tiny, tbs, c.s);
-    block_mult(P->V1.p, nullptr, {}, P->Rinv.p, P->Rinv.bs, tiny, tbs, seed + 1, P->V1.p, ritz ? P->blkP.p : nullptr,
-               pbs, first, second, q, c.s);
+               nullptr, 0, drop, c.s);
+    block_mult(P->V1.p, nullptr, {}, P->Rinv.p, P->Rinv.bs, nullptr, 0, drop, seed + 1, P->V1.p,
+               ritz ? P->blkP.p : nullptr, pbs, first, second, q, c.s);
     if (!ritz) return;
     np = block_reduce(P->blkP.p, pbs, second, q, c.s);
-    block_chol(P->blkP.p, pbs, np, b, nb, 0.0, false, P->Rinv.p, P->Rinv.bs, P->flags.p, second, nullptr, 0.0, tiny,
-               tbs, c.s);
-    block_mult(P->V1.p, nullptr, {}, P->Rinv.p, P->Rinv.bs, tiny, tbs, seed + 2, P->V1.p, nullptr, pbs, second, nullptr,
-               q, c.s);
+    block_chol(P->blkP.p, pbs, np, b, nb, 0.0, false, P->Rinv.p, P->Rinv.bs, P->flags.p, second, nullptr, 0.0, nullptr,
+               0, drop, c.s);
+    block_mult(P->V1.p, nullptr, {}, P->Rinv.p, P->Rinv.bs, nullptr, 0, drop, seed + 2, P->V1.p, nullptr, pbs, second,
+               nullptr, q, c.s);
 }
 
 // the n x b block X (V1 or Y1) orthonormalised into V1

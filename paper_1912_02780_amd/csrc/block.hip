@@ -452,6 +452,12 @@ __global__ __launch_bounds__(256) void block_reduce_kernel(double* part, i64 p_b
 // columns: 2^-53 x 96 = 2^-46.4, and the explicit inverses of the tiles add to it).
 constexpr double kDependent = 0x1p-42;
 
+__device__ inline void wave_sync() {   // LDS stores of this wave's lanes before loads by others of them
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 __device__ inline double rsqrt64(double d) {
     double r = __builtin_amdgcn_rsq(d);
     r *= 1.5 - 0.5 * d * r * r;
@@ -614,6 +620,7 @@ __global__ __launch_bounds__(256) void block_chol_kernel(const double* __restric
         if (kb + 1 == T) break;
         if (w == 0) {
             put(A, kb + 1, kb + 1, product(A, kb + 1, kb, A, kb + 1, kb, true, -1.0, tile(A, kb + 1, kb + 1)));
+            wave_sync();   // its lanes read what others of them have just stored
             diagonal(kb + 1);
         } else {
             int turn = 0;

@@ -78,7 +78,12 @@ std::mutex& slot_mutex() {
     return *m;
 }
 std::vector<char*>& free_slots() {
-    static std::vector<char*>* v = new std::vector<char*>;
+    // with room for all that are kept: releasing one does not allocate (and throw)
+    static std::vector<char*>* v = [] {
+        auto* list = new std::vector<char*>;
+        list->reserve(kHostSlotsKept);
+        return list;
+    }();
     return *v;
 }
 }  // namespace
@@ -95,9 +100,11 @@ HostSlot::HostSlot() {
     // allowed also while another thread captures a graph
     hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
     const bool exchanged = hipThreadExchangeStreamCaptureMode(&mode) == hipSuccess;
-    if (hipHostMalloc((void**)&p, kHostSlotBytes, hipHostMallocPortable) != hipSuccess) p = nullptr;
+    if (hipHostMalloc((void**)&p, kHostSlotBytes, hipHostMallocPortable) != hipSuccess) {
+        p = nullptr;
+        (void)hipGetLastError();   // this error only, not one that was there before
+    }
     if (exchanged) (void)hipThreadExchangeStreamCaptureMode(&mode);
-    (void)hipGetLastError();
 }
 
 HostSlot::~HostSlot() {

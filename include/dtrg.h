@@ -315,6 +315,13 @@ dtrg_status dtrg_isometry_optimize(dtrg_plan* plan, const double* T0_dev, int la
  * isometry reports iters = -1 and zero spectrum fields. */
 dtrg_status dtrg_plan_step_info(const dtrg_plan* plan, int k, dtrg_step_info* info);
 
+/* The subspace iteration of step k (1 <= k <= n_steps) in the last forward pass that chose its
+ * schedule: products with the Gram and the Rayleigh-Ritz solves among them (see rr_skip), over all
+ * blocks where the eigenpairs are found block by block.  Both 0 where the step does not iterate (its
+ * whole spectrum, a given isometry, or nothing truncated).  With side_rule 1: those of the unfolding
+ * that was kept. */
+dtrg_status dtrg_plan_step_solves(const dtrg_plan* plan, int k, int* products_host, int* solves_host);
+
 /*
  * HIP-event timing of the chi^7 join contraction (the O(D^7) term of the step: the upper copy
  * times the left isometry joined with the lower copy over (x2, j); launched once per step in the

@@ -25,7 +25,7 @@ DTRG_FP64, DTRG_FP32, DTRG_BF16X3, DTRG_BF16X6 = 0, 1, 2, 3
 PRECISIONS = {"fp64": DTRG_FP64, "fp32": DTRG_FP32, "bf16x3": DTRG_BF16X3, "bf16x6": DTRG_BF16X6}
 
 EXPORTED = ["dtrg_default_options", "dtrg_hotrg_forward", "dtrg_plan_create", "dtrg_plan_forward",
-            "dtrg_hotrg_backward", "dtrg_plan_step_info", "dtrg_plan_profile", "dtrg_batch_create", "dtrg_batch_run",
+            "dtrg_hotrg_backward", "dtrg_plan_step_info", "dtrg_plan_step_solves", "dtrg_plan_profile", "dtrg_batch_create", "dtrg_batch_run",
             "dtrg_hotrg_batched",
             "dtrg_batch_step_info", "dtrg_batch_profile", "dtrg_batch_device_bytes", "dtrg_batch_destroy", "dtrg_tuned_shapes",
             "dtrg_plan_device_bytes", "dtrg_plan_destroy", "dtrg_last_error", "dtrg_contract", "dtrg_contract_config", "dtrg_version",
@@ -84,6 +84,8 @@ def _load():
     lib.dtrg_hotrg_backward.restype = c_int
     lib.dtrg_plan_step_info.argtypes = [c_void_p, c_int, POINTER(StepInfo)]
     lib.dtrg_plan_step_info.restype = c_int
+    lib.dtrg_plan_step_solves.argtypes = [c_void_p, c_int, POINTER(c_int), POINTER(c_int)]
+    lib.dtrg_plan_step_solves.restype = c_int
     lib.dtrg_batch_create.argtypes = [c_int, c_int, POINTER(c_int), c_int, POINTER(Options), POINTER(c_void_p)]
     lib.dtrg_batch_create.restype = c_int
     lib.dtrg_batch_run.argtypes = [c_void_p, c_void_p, c_void_p, c_double, POINTER(c_double), c_void_p,
@@ -220,6 +222,12 @@ class Plan:
         info = StepInfo()
         _check(lib.dtrg_plan_step_info(self._h, k, byref(info)))
         return info.as_dict()
+
+    def step_solves(self, k: int) -> tuple[int, int]:
+        """(products with the Gram, Rayleigh-Ritz solves among them) of step k's subspace iteration."""
+        products, solves = c_int(), c_int()
+        _check(lib.dtrg_plan_step_solves(self._h, k, byref(products), byref(solves)))
+        return products.value, solves.value
 
     def profile(self, reset: bool = True):
         """(launches, total_ms, flops) of the timed chi^7 contractions since the last reset."""

@@ -588,6 +588,18 @@ dtrg_status dtrg_isometry_optimize(dtrg_plan* plan, const double* T0_dev, int la
     }
 }
 
+dtrg_status dtrg_plan_step_solves(const dtrg_plan* plan, int k, int* products_host, int* solves_host) {
+    g_last_error.clear();
+    if (!plan || !products_host || !solves_host) { g_last_error = "NULL argument"; return DTRG_EINVAL; }
+    if (!plan->fwd_ok) { g_last_error = "plan has no successful forward"; return DTRG_ESTATE; }
+    if (k < 1 || k > plan->nsteps) { g_last_error = "step index out of range"; return DTRG_EINVAL; }
+    const StepCk& st = plan->steps[k - 1];
+    const bool iterates = !st.fixed && !st.sh.ident && !st.sh.full;
+    *products_host = iterates ? st.iters : 0;
+    *solves_host = iterates ? st.solves : 0;
+    return DTRG_OK;
+}
+
 dtrg_status dtrg_plan_step_info(const dtrg_plan* plan, int k, dtrg_step_info* info) {
     g_last_error.clear();
     if (!plan || !info) { g_last_error = "NULL argument"; return DTRG_EINVAL; }

@@ -789,6 +789,7 @@ void eigensolve_locked(Ctx& c, StepCk& st, int k, const StepCk* warm) {
     std::vector<double> resh((size_t)nb * P->res.bs), thh((size_t)nb * P->th.bs);
     const BlockCut q = block_cut(n, bw, nb, vbs);
     int total = 0;
+    st.solves = 0;
     for (int blk = 0; blk < nblk; ++blk) {
         const int c0 = blk * er;
         const bool last = blk == nblk - 1;
@@ -816,6 +817,7 @@ void eigensolve_locked(Ctx& c, StepCk& st, int k, const StepCk* warm) {
             }
             deflate(c, st.U.p, b, ubs, c0, P->Y1.p, bw, vbs, n);
             rayleigh_ritz(c, q, nullptr, nullptr);
+            ++st.solves;
             Readback back(P);
             back.add(resh.data(), P->res.p, resh.size() * sizeof(double));
             if (rr.open(P, it, warm_used)) back.add(thh.data(), P->th.p, thh.size() * sizeof(double));
@@ -870,7 +872,7 @@ void eigensolve(Ctx& c, StepCk& st, int k, const StepCk* warm) {
         // Rayleigh-Ritz solves below are checked through the Ritz residuals instead)
         jacobi_psd(P->Gw.p, n, n, P->Gw.bs, 1, 0, st.lam.p, st.lam.bs, st.U.p, n, st.U.bs, nb, kJacobiSweeps, c.s,
                    P->flags.p, kFlagJacobi);
-        st.iters = 0;
+        st.iters = st.solves = 0;
         return;
     }
     if (st.sh.lock_n) {
@@ -900,6 +902,7 @@ void eigensolve(Ctx& c, StepCk& st, int k, const StepCk* warm) {
     RitzPlan rr;
     rr.stride = c.adaptive() ? 1 : st.rr_stride;
     rr.from = c.adaptive() ? it_max : st.rr_from;
+    if (c.adaptive()) st.solves = 0;
     for (it = 1; it <= it_max; ++it) {
         const uint64_t noise = seed + 7919ULL * it;
         bool shifted = false;
@@ -919,6 +922,7 @@ void eigensolve(Ctx& c, StepCk& st, int k, const StepCk* warm) {
         }
         rayleigh_ritz(c, q, W, &sh);
         if (c.adaptive()) {
+            ++st.solves;
             Readback back(P);
             back.add(resh.data(), P->res.p, resh.size() * sizeof(double));
             if (rr.open(P, it, warm_used)) back.add(thh.data(), P->th.p, thh.size() * sizeof(double));
@@ -985,7 +989,7 @@ void eigensolve_sides(Ctx& c, StepCk& st, int k, const StepCk* warm) {
     gram_of_step(c, st, k, true);
     check_flags(P, kFlagNonPos | kFlagNonFinite, where + " (right unfolding)");
     eigensolve(c, st, k, warm);
-    const int iters_right = st.iters;
+    const int iters_right = st.iters, solves_right = st.solves;
     st.tw_right = host_trunc_weight(c, st);
     copy2d(st.U.p, b, st.U.bs, P->side_U.p, b, P->side_U.bs, n, b, nb, c.s);
     copy2d(st.lam.p, b, st.lam.bs, P->side_lam.p, b, P->side_lam.bs, 1, b, nb, c.s);
@@ -1001,6 +1005,7 @@ void eigensolve_sides(Ctx& c, StepCk& st, int k, const StepCk* warm) {
         copy2d(P->side_lam.p, b, P->side_lam.bs, st.lam.p, b, st.lam.bs, 1, b, nb, c.s);
         for (int i = 0; i < 3; ++i) copy2d(P->sp(9 + i), 1, P->S, P->sc(k, slots[i]), 1, P->S, 1, 1, nb, c.s);
         st.iters = iters_right;
+        st.solves = solves_right;
         if (st.keep_gram) gram_of_step(c, st, k, true);
     }
     if (st.keep_gram) keep_gram(c, st, true);

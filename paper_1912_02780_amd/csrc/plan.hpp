@@ -107,7 +107,8 @@ struct StepCk {
     DevBuf<double> Ak, Bk, Gk;
     OpBuf P1k, Q2k;
     // schedule (written by adaptive passes, replayed by fixed passes)
-    int iters = 0;         // subspace iterations
+    int iters = 0;         // subspace iterations (products with the Gram)
+    int solves = 0;        // Rayleigh-Ritz solves among them (adaptive passes count, fixed ones repeat them)
     int rr_stride = 1;     // Gram products per Rayleigh-Ritz solve of the subspace iteration, from
     int rr_from = 0;       // this product on (a solve after every product up to it)
     int cheb = 0;          // degree of the complement expansion (0: none)

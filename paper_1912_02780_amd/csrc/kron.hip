@@ -11,8 +11,9 @@
 // d is split to give every compute unit about four workgroups, and a second kernel adds the parts up.
 // Measured there: 110 us and 10 for the sum, 49 TFLOP/s (148 with selects on the loaded values, which made each
 // load wait for the one before).
-// Y^2 = 16 only: with 4 the tile would hold four a and the sums 4 X columns.  Above X = 128 A[a] and the sums do
-// not fit the registers; those sizes keep the two contractions.
+// Y^2 = 16 only: the tile is jk x alpha, and 4 or 9 values of jk would leave three quarters or half of its rows empty
+// (or want several a in it, another layout of A and of the sums).  Above X = 128 A[a] and the sums do not fit the
+// registers.  Those sizes keep the two contractions; up to X = 2 Y^2 = 32 the Gram is formed.
 #include <algorithm>
 #include <type_traits>
 
@@ -127,7 +128,7 @@ __global__ __launch_bounds__(256) void kron_sum_kernel(const double* __restrict_
 
 }  // namespace
 
-bool kron_product_fits(int X, int YY) { return YY == 16 && X >= 1 && X <= 128; }
+bool kron_product_fits(int X, int YY) { return YY == 16 && X > 32 && X <= 128; }
 
 void kron_product(const double* A, i64 a_bs, const double* B, i64 b_bs, const double* V, i64 v_bs, double* W, i64 w_bs,
                   const double* s_dev, i64 s_bs, double* C, i64 c_bs, int X, int w, int nb, hipStream_t s) {
@@ -145,8 +146,6 @@ void kron_product(const double* A, i64 a_bs, const double* B, i64 b_bs, const do
                            parts, per);
     };
     switch ((X + 15) / 16) {
-        case 1: go(std::integral_constant<int, 1>()); break;
-        case 2: go(std::integral_constant<int, 2>()); break;
         case 3: go(std::integral_constant<int, 3>()); break;
         case 4: go(std::integral_constant<int, 4>()); break;
         case 5: go(std::integral_constant<int, 5>()); break;

@@ -295,9 +295,11 @@ dtrg_status dtrg_hotrg_backward(dtrg_plan* plan, double gbar, double* T0bar_dev,
  *   nullable), then n_sweeps sweeps over the first `layers` steps whose isometry truncates (a
  *   scheme-(b) plan: the last `layers`, the optimisation depth below the final temperature)
  *   (chi' < X^2), from the finest scale up; per sweep and step, n_inner MERA updates, each a
- *   backward pass for the isometry gradient, the polar factor w <- U V^T (computed on the device
- *   without squaring the gradient's condition number), and a forward pass with the new isometry;
- *   the isometries above the optimised steps remain HOTRG's local ones, recomputed every pass.
+ *   backward pass down to that step for the isometry gradient, the polar factor w <- U V^T (computed
+ *   on the device without squaring the gradient's condition number), and a forward pass with the new
+ *   isometry from that step on, whose input is kept (plans with side_rule run whole forward passes);
+ *   the isometries above the optimised steps remain HOTRG's local ones, recomputed in every forward
+ *   pass from the vectors of the one before.
  *   ln Z / N after every update goes to history_host (host, n_sweeps * layers * n_inner doubles,
  *   nullable), the last to *lnZ_host.  The optimised isometries stay fixed in the plan, whose last
  *   forward pass is valid (a backward pass may follow).  The optimised steps need chi' <= 80 and
@@ -328,9 +330,11 @@ dtrg_status dtrg_plan_step_solves(const dtrg_plan* plan, int k, int* products_ho
  * forward and once more in the backward's recompute) recorded since the last reset on a plan
  * created with opt.profile = 1: number of launches, summed milliseconds and summed algorithmic
  * flops (2 M N K per launch).  Only launches in the plan's contraction precision with outputs of at
- * least 256 x 128 are timed (bf16 planes: on the 128 x 128 tile or a larger one).  Scheme (b) plans (whose passes the eigensolver dominates) time instead every
- * product with a step's Gram (the subspace iteration's and the eigen-adjoint's, FP64; in Kronecker
- * form two contractions each).  Synchronises on the recorded events; reset != 0 clears the record.
+ * least 256 x 128 are timed (bf16 planes: on the 128 x 128 tile or a larger one).  Scheme (b) plans
+ * (whose passes the eigensolver dominates) time instead every product with a step's Gram (the
+ * subspace iteration's and the eigen-adjoint's, FP64; in Kronecker form one launch and a sum with a
+ * physical dimension of 4 up to X = 128, two contractions otherwise).  Synchronises on the recorded
+ * events; reset != 0 clears the record.
  */
 dtrg_status dtrg_plan_profile(dtrg_plan* plan, long long* launches, double* total_ms, double* flops, int reset);
 

@@ -727,9 +727,14 @@ void rayleigh_ritz(Ctx& c, const BlockCut& q, const double* W, const BlockShift*
 // x = 2 lambda / theta_{b-1} - 1 the pair of lambda gains T_stride(x) on them where the one shift gains x^stride
 // (x = 4: 1921 against 256, x = 1.6: 33 against 6.6), and G alone ((x + 1) / 2)^stride.  Largest zero first,
 // so that rounding of a product whose shift is close to a wanted pair is damped by those that follow.
+// The block-locked solve applies that from the solve that takes the stride up on.  In eigensolve the block built by
+// that very solve has its shift from before the decision (half of theta_{b-1}, or scheme (b)'s 2^-45), so that the first
+// cycle gains 5.9 and 190 (4.8 and 119) for x = 1.6 and 4, a little less than four single shifts, and only those
+// after it 33 and 1921.
 // Measured: XY chain, D = 32, 18 steps: 216 products and solves -> 175 and 109 (62 -> 44 ms); D = 96, blocks of
-// 96 columns of a 9216 x 9216 Gram in Kronecker form: 471 -> 477 and 228 (446 -> 337 ms), the residuals of the
-// last steps, which stalled at 1e-12, at 1e-15; Ising, chi = 32, at criticality: 377 and 137 -> 352 and 113.
+// 96 columns of a 9216 x 9216 Gram in Kronecker form: 476 products and solves -> 369 products, 351 -> 221 ms, the
+// residuals of the last steps, which stalled at 1e-12, at 1e-14 and below; Ising, chi = 32, at criticality: 364
+// products and solves -> 371 and 119.
 struct RitzPlan {
     int stride = 1, from = 0;
     bool solve(int it, int it_max) const { return it <= from || (it - from) % stride == 0 || it == it_max; }

@@ -151,7 +151,8 @@ GemmCfg gemm_resolve(Prec prec, const GemmOp& op) {
         const i64 part = std::max<i64>(1, nz * op.M * op.N * (prec == Prec::F64 ? 8 : 4));
         int fill = 1, least = gemm_chain_splits(prec, op);
         if (tiles < 512)
-            fill = (int)std::min<i64>({(1024 + tiles - 1) / tiles, std::max<i64>(1, op.K / (bk_of(prec, pick.tile) * 8)), 64});
+            fill = (int)std::min<i64>({(1024 + tiles - 1) / tiles, std::max<i64>(1, op.K / (bk_of(prec, pick.tile) * 8)), 64,
+                                       std::max<i64>(1, kMaxSplitBytes / part)});
         if (prec == Prec::F32) {
             // The length of an FP32 chain sets its rounding: chains are never longer than the rule makes them, and
             // where the output does not fill the chip anyway no longer than 1024 products as far as the

@@ -57,13 +57,16 @@ int out_code(Prec prec, Out out) {
 i64 round8(i64 x) { return (x + 7) / 8 * 8; }
 
 // K chunk and number of K chunks a resolved configuration runs with (chunks are whole K tiles)
-void resolve_chunks(Prec prec, const GemmOp& op, const GemmCfg& cfg, int& k_chunk, int& splits) {
-    const int BK = bk_of(prec, cfg.tile);
-    splits = std::max(1, cfg.splits);
-    const int k_chunk_raw = (op.K + splits - 1) / splits;
+void chunks_of(int K, int BK, int want, int& k_chunk, int& splits) {
+    splits = std::max(1, want);
+    const int k_chunk_raw = (K + splits - 1) / splits;
     k_chunk = std::max(BK, ((k_chunk_raw + BK - 1) / BK) * BK);
-    splits = std::max(1, (op.K + k_chunk - 1) / k_chunk);
-    if (op.K == 0) splits = 1;
+    splits = std::max(1, (K + k_chunk - 1) / k_chunk);
+    if (K == 0) splits = 1;
+}
+
+void resolve_chunks(Prec prec, const GemmOp& op, const GemmCfg& cfg, int& k_chunk, int& splits) {
+    chunks_of(op.K, bk_of(prec, cfg.tile), cfg.splits, k_chunk, splits);
 }
 
 // a short, wide split-bf16 output is computed as its transpose (see gemm)
@@ -105,26 +108,34 @@ namespace {
 // on one XCD, two to a unit, and not 62 on 256.
 // The numbers are a fit to 420 random outputs (16 to 40000 x 16 to 8192, K 16 to 40000, every layout, up to 64
 // chunks); on those and 160 others, 7000 runs a type, it is 6% off in FP64 and 8% in FP32 (mean).
-double tile_time(Prec prec, const GemmOp& op, int tile, int splits) {
-    int k_chunk = 0, s = 1;
-    GemmCfg c;
-    c.tile = tile;
-    c.splits = splits;
-    resolve_chunks(prec, op, c, k_chunk, s);
-    const i64 nz = (i64)op.batch * op.batch2;
-    const i64 tiles = (tile_count(op, tile_rows(tile), tile_cols(tile)) + kXcds - 1) / kXcds;
-    const i64 n = (tiles * nz * s + 31) / 32;   // blocks of the busiest unit
-    const double steps = (double)(k_chunk / bk_of(prec, tile));
+// What does not depend on the count is worked out once: the choice tries up to forty counts on every launch.
+struct TileTime {
     struct Cost { double launch, wait, step; };
-    const Cost f64[2] = {{5.8, 0.62, 0.52}, {6.9, 0.44, 1.94}}, f32[2] = {{6.1, 0.44, 0.29}, {7.8, 0.46, 1.17}};
-    const Cost q = (prec == Prec::F64 ? f64 : f32)[tile - 1];
-    const int full = tile == 2 ? 2 : 4;
-    const i64 rest = n % full;
-    double t = q.launch + steps * ((double)(n / full) * (q.wait + full * q.step) + (rest ? q.wait + rest * q.step : 0.0));
-    const double out = (double)op.M * op.N * nz;
-    if (s > 1) t += prec == Prec::F64 ? 1.9 + (s + 1) * out * 8.0 / 3.9e6 : 2.8 + (s + 1) * out * 4.0 / 3.2e6;
-    return t;
-}
+    Cost q;
+    i64 tiles;                 // of the busiest XCD in one chunk
+    double sum_launch, sum;    // the pass over the partials: its launch, and one partial read or written
+    int K, bk, lg;             // 2^lg blocks of a unit run at a time
+
+    TileTime(Prec prec, const GemmOp& op, int tile) : K(op.K), bk(bk_of(prec, tile)), lg(tile == 2 ? 1 : 2) {
+        constexpr Cost f64[2] = {{5.8, 0.62, 0.52}, {6.9, 0.44, 1.94}}, f32[2] = {{6.1, 0.44, 0.29}, {7.8, 0.46, 1.17}};
+        const i64 nz = (i64)op.batch * op.batch2;
+        const bool d = prec == Prec::F64;
+        q = (d ? f64 : f32)[tile - 1];
+        tiles = (tile_count(op, tile_rows(tile), tile_cols(tile)) + kXcds - 1) / kXcds * nz;
+        sum = (double)op.M * op.N * nz * (d ? 8.0 / 3.9e6 : 4.0 / 3.2e6);
+        sum_launch = d ? 1.9 : 2.8;
+    }
+    double operator()(int splits) const {
+        int k_chunk = 0, s = 1;
+        chunks_of(K, bk, splits, k_chunk, s);
+        const i64 n = (tiles * s + 31) >> 5;   // blocks of the busiest unit
+        const int full = 1 << lg, rest = (int)(n & (full - 1));
+        const double steps = (double)(k_chunk / bk);
+        double t = q.launch + steps * ((double)(n >> lg) * (q.wait + full * q.step) + (rest ? q.wait + rest * q.step : 0.0));
+        if (s > 1) t += sum_launch + (s + 1) * sum;
+        return t;
+    }
+};
 
 // the largest split-K workspace (bytes) the choice may spend: that of 1024 blocks of 128 x 128 in FP64
 constexpr i64 kMaxSplitBytes = 128LL << 20;
@@ -164,7 +175,8 @@ GemmCfg gemm_resolve(Prec prec, const GemmOp& op) {
                 least = (int)std::max<i64>(least, std::min<i64>({(op.K + 1023) / 1024, kMaxSplitBytes / part, 64, 65535 / nz}));
         }
         if (pick.splits <= 0) pick.splits = std::max(fill, least);
-        const double base = tile_time(prec, op, pick.tile, pick.splits);
+        const TileTime time[2] = {TileTime(prec, op, 1), TileTime(prec, op, 2)};
+        const double base = time[pick.tile - 1](pick.splits);
         double best = (std::min(op.M, op.N) >= 256 ? kChoiceMarginWide : kChoiceMargin) * base;
         for (int tile = 1; tile <= 2; ++tile) {
             if (op.cfg.tile != 0 && op.cfg.tile != tile) continue;
@@ -172,7 +184,7 @@ GemmCfg gemm_resolve(Prec prec, const GemmOp& op) {
             const int lo = op.cfg.splits > 0 ? op.cfg.splits : least;
             const int hi = op.cfg.splits > 0 ? op.cfg.splits : (int)std::max<i64>(least, most);
             for (int s = lo; s <= hi; s += 1 + s / 8) {
-                const double t = tile_time(prec, op, tile, s);
+                const double t = time[tile - 1](s);
                 if (t < best) {
                     best = t;
                     pick.tile = tile;
@@ -184,9 +196,9 @@ GemmCfg gemm_resolve(Prec prec, const GemmOp& op) {
             // the shortest chains that cost no more than 5%: chi = 16 gradients are 4.1e-7 off FP64 with chains of
             // 64 and 5.3e-7 with 128, which 4096 x 256 x 256 would take otherwise, in the same time
             const i64 most = std::min<i64>({64, op.K / (bk_of(prec, pick.tile) * 4), kMaxSplitBytes / part, 65535 / nz});
-            const double limit = 1.05 * tile_time(prec, op, pick.tile, pick.splits);
+            const double limit = 1.05 * time[pick.tile - 1](pick.splits);
             for (int s = pick.splits; s <= most; s += 1 + s / 8)
-                if (tile_time(prec, op, pick.tile, s) <= limit) pick.splits = s;
+                if (time[pick.tile - 1](s) <= limit) pick.splits = s;
         }
         return pick;
     }

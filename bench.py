@@ -86,10 +86,10 @@ TRAFFIC_SOURCES = ["paper_1912_02780_amd/csrc/gemm_kernels.hpp", "paper_1912_027
                    "paper_1912_02780_amd/csrc/gemm_f32.hip", "paper_1912_02780_amd/csrc/gemm_split.hpp"]
 MEASURED_TRAFFIC = {
     # chi^7 join at chi = 48 (M = 110592, N = 2304, K = 2304), 20 launches of that size per pass
-    ("chi48", "bf16x6"): {"sources_sha256": "6cedb386caa7edc605232b1bb8f6c0a96a531ee157b4eee9f43039476da4f72c",
-                          "fetch_kib": 5296750.0, "write_kib": 1700570.0,
+    ("chi48", "bf16x6"): {"sources_sha256": "604faabc80d9101ec05a440f40fd862122e76fdf880546a433dcd55b9334598f",
+                          "fetch_kib": 5332400.0, "write_kib": 1701000.0,
                           # SQ_VALU_MFMA_BUSY_CYCLES / (GRBM_GUI_ACTIVE per XCD x 1024 SIMDs), same runs
-                          "mfma_busy_counter": 0.575},
+                          "mfma_busy_counter": 0.574},
 }
 
 
